@@ -185,8 +185,10 @@ ago_status ago_fused_conv_chain(const void* x, const void* wa, const float* ba,
 
 /* matmul -> matmul (pw->pw; a matrix product is a pointwise convolution, Sec. III-B):
  *   y = act(x w1 + b1) w2 + b2
- * x:[M,K] w1:[K,F] w2:[F,K2] y:[M,K2].  bf16 only.  The hidden activation never
- * leaves the chip; partial sums over slices of F go through `workspace`.
+ * x:[M,K] w1:[K,F] w2:[F,K2] y:[M,K2].  bf16 only.  The fused kernel keeps the hidden
+ * activation on chip and passes partial sums over slices of F through `workspace`; where two
+ * products are predicted faster (more than one slice, K and F multiples of 32) the built-in
+ * choice runs those, with the hidden tensor in the same workspace.
  * Requires K % 64 == 0, F % 8 == 0, K2 % 8 == 0 (else UNSUPPORTED); F and K2 need not be multiples of
  * the kernel's 384-wide hidden slices and column blocks. */
 ago_status ago_fused_ffn(const void* x, const void* w1, const float* b1,
@@ -212,13 +214,12 @@ ago_status ago_fused_ffn(const void* x, const void* w1, const float* b1,
  * through LDS; results agree with ago_fused_ffn up to the order of the fp32 summation. */
 /* The un-fused counterparts on packed weights (Fig. 3 / Fig. 4: one kernel per complex operator, its bias and
  * activation in the epilogue), so that fused and un-fused can be compared on the same weight layout:
- *   ago_gemm_packed          c = act(a wp + bias), a:[M,K] c:[M,N] bf16 row-major, wp = packed [K,N].  Tilings:
- *                            128 x 192 (needs N % 192 == 0, K % 128 == 0) or 64 x 96 with the reduction split
- *                            over the waves (N % 96 == 0, K % 512 == 0); other shapes UNSUPPORTED.
+ *   ago_gemm_packed          c = act(a wp + bias), a:[M,K] c:[M,N] bf16 row-major, wp = packed [K,N].  Requires
+ *                            N % 192 == 0 and K % 128 == 0, or N % 96 == 0 and K % 512 == 0 (else UNSUPPORTED).
  *   ago_unfused_ffn_packed   the chain as two such products; workspace = the hidden tensor,
  *                            ago_workspace_bytes(AGO_OP_UNFUSED_FFN, {M,K,F,K2}). */
 size_t ago_packed_weight_bytes(int K, int N);
-/* Host-only: 1 when ago_gemm_packed has a tiling for an [M,K] x [K,N] product, else 0. */
+/* Host-only: 1 when ago_gemm_packed takes an [M,K] x [K,N] product, else 0. */
 int ago_gemm_packed_supported(int M, int K, int N);
 ago_status ago_gemm_packed(const void* a, const void* wp, const float* bias, void* c,
                            int M, int K, int N, ago_act act, ago_dtype dt, void* hip_stream);

@@ -24,7 +24,10 @@ SOURCES = [
     "ago_api.hip",
     "ago_elementwise.hip",
     "ago_gemm.hip",
-    "ago_gemm_packed.hip",
+    "ago_gemm_dma.hip",
+    "ago_gemm_dma_rows.hip",
+    "ago_gemm_dma_packed.hip",
+    "ago_gemm_dma_special.hip",
     "ago_conv.hip",
     "ago_fused_invres.hip",
     "ago_fused_conv_chain.hip",

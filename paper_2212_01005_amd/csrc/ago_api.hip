@@ -358,14 +358,14 @@ ago_status ago_pack_weight(const void* w, void* wp, int K, int N, ago_dtype dt, 
 }
 
 int ago_gemm_packed_supported(int M, int K, int N) {
-    return (M > 0 && K > 0 && N > 0 && gemm_packed_variant(M, K, N) != 0) ? 1 : 0;
+    return (M > 0 && K > 0 && N > 0 && gemm_packed_ok(K, N)) ? 1 : 0;
 }
 
 ago_status ago_gemm_packed(const void* a, const void* wp, const float* bias, void* c, int M, int K, int N,
                            ago_act act, ago_dtype dt, void* hip_stream) {
     ago_status st = check_gemm_packed(a, wp, c, bias, M, K, N, act, dt);
     if (st != AGO_OK) return st;
-    return from_hip(gemm_packed(a, wp, bias, c, M, K, N, act, as_stream(hip_stream)));
+    return from_hip(gemm_dma(a, wp, true, bias, nullptr, c, M, K, N, act, as_stream(hip_stream)));
 }
 
 ago_status ago_unfused_ffn_packed(const void* x, const void* w1p, const float* b1, const void* w2p,
@@ -378,7 +378,7 @@ ago_status ago_unfused_ffn_packed(const void* x, const void* w1p, const float* b
     if (st != AGO_OK) return st;
     if (workspace_bytes == 0 || !workspace) return AGO_ERR_WORKSPACE;
     // both products are checked before the first is launched
-    if (gemm_packed_variant(M, K, F) == 0 || gemm_packed_variant(M, F, K2) == 0) return AGO_ERR_UNSUPPORTED;
+    if (!gemm_packed_ok(K, F) || !gemm_packed_ok(F, K2)) return AGO_ERR_UNSUPPORTED;
     st = ago_gemm_packed(x, w1p, b1, workspace, M, K, F, act, dt, s);
     if (st != AGO_OK) return st;
     return ago_gemm_packed(workspace, w2p, b2, y, M, F, K2, AGO_ACT_NONE, dt, s);

@@ -17,6 +17,7 @@
 //   barrier per tile.  Two register sets and two LDS buffers alternate (loop unrolled by two).
 #include "ago_dev.hpp"
 #include "ago_launch.hpp"
+#include "ago_host.hpp"
 
 namespace ago {
 
@@ -369,7 +370,15 @@ int fused_ffn_nsplit(int cfg, int F) {
 hipError_t fused_ffn(const void* x, const void* w1, const float* b1, const void* w2, const float* b2,
                      void* y, int M, int K, int F, int K2, int act, int tile_cfg, void* workspace,
                      hipStream_t s) {
-    switch (fused_ffn_pick_cfg(M, K, F, K2, tile_cfg)) {
+    const int cfg = fused_ffn_pick_cfg(M, K, F, K2, tile_cfg);
+    const int ns = fused_ffn_nsplit(cfg, F);
+    if (tile_cfg < 0 && ns > 1) {          // the built-in choice may run the chain as two products in the same workspace
+        FfnPlan plan;
+        if (plan_ffn(M, K, F, K2, &plan) &&
+            ffn_two_products_pay(M, K, F, K2, false, (size_t)ns * M * K2 * 4, plan.predicted_us))
+            return ffn_two_products(x, w1, b1, w2, b2, y, M, K, F, K2, act, false, workspace, s);
+    }
+    switch (cfg) {
         case 0: return launch_ffn<128, 192, 128>(x, w1, b1, w2, b2, y, M, K, F, K2, act, workspace, s);
         case 1: return launch_ffn<128, 128, 128>(x, w1, b1, w2, b2, y, M, K, F, K2, act, workspace, s);
         case 2: return launch_ffn<128, 64, 128>(x, w1, b1, w2, b2, y, M, K, F, K2, act, workspace, s);

@@ -24,6 +24,7 @@
 // requested before the activation is evaluated).
 #include "ago_dev.hpp"
 #include "ago_launch.hpp"
+#include "ago_host.hpp"
 #include <type_traits>
 
 namespace ago {
@@ -334,6 +335,11 @@ static hipError_t launch_packed(const void* x, const void* w1p, const float* b1,
 hipError_t fused_ffn_packed(const void* x, const void* w1p, const float* b1, const void* w2p, const float* b2,
                             void* y, int M, int K, int F, int K2, int act, void* workspace, hipStream_t s) {
     if (!fused_ffn_packed_ok(M, K, F, K2)) return hipErrorInvalidValue;
+    const int nsplit = fused_ffn_packed_nsplit(F);
+    FfnPlan plan;                          // the row-major kernel's time; this one takes about 0.88 of it
+    if (nsplit > 1 && plan_ffn(M, K, F, K2, &plan) &&
+        ffn_two_products_pay(M, K, F, K2, true, (size_t)nsplit * fused_ffn_packed_rows(M) * K2 * 4, 0.88 * plan.predicted_us))
+        return ffn_two_products(x, w1p, b1, w2p, b2, y, M, K, F, K2, act, true, workspace, s);
     const bool ragged = F % kFS != 0 || K2 % kCB != 0;
     const bool deep = K % 128 == 0 && F % 128 == 0 && (F % kFS) % 128 == 0;   // k-steps in fours everywhere
     if (deep) {

@@ -125,6 +125,14 @@ __global__ __launch_bounds__(256) void fused_qkv_kernel(const QkvParams p) {
 hipError_t fused_qkv(const void* x, const void* wq, const void* wk, const void* wv, const float* bq,
                      const float* bk, const float* bv, void* q, void* k, void* v, int B, int S, int K, int Hh,
                      int D, int head_major, hipStream_t s) {
+    // whole 32-deep steps (and head-major stores in 16-byte pieces): the direct-to-LDS kernels; the kernel above covers
+    // the other sizes (8 x 384 x 768 -> 3 x 768: 36 us against 22 us)
+    if (gemm_dma_ok(K, Hh * D, false) && (!head_major || D % 8 == 0)) {
+        const void* w[3] = {wq, wk, wv};
+        const float* b[3] = {bq, bk, bv};
+        void* o[3] = {q, k, v};
+        return gemm_dma_qkv(x, w, b, o, B, S, K, Hh, D, head_major != 0, s);
+    }
     QkvParams p;
     p.x = (const bf16_t*)x;
     p.w[0] = (const bf16_t*)wq; p.w[1] = (const bf16_t*)wk; p.w[2] = (const bf16_t*)wv;

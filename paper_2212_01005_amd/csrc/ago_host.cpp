@@ -15,7 +15,7 @@ int fused_ffn_nsplit(int cfg, int F);
 bool fused_ffn_packed_ok(int M, int K, int F, int K2);
 long fused_ffn_packed_rows(int M);
 int fused_ffn_packed_nsplit(int F);
-int gemm_packed_variant(int M, int K, int N);
+bool gemm_packed_ok(int K, int N);
 size_t fused_invres_workspace(int N, int H, int W, int Cin, int Cexp, int Cout, int stride, int ksize, bool bf16,
                               int tile_cfg, int mode);
 
@@ -146,7 +146,7 @@ ago_status check_gemm_packed(const void* a, const void* wp, const void* c, const
     const void* ps[4] = {a, wp, c, bias};
     for (const void* p : ps)
         if (p && !aligned16(p)) return AGO_ERR_ALIGN;
-    if (dt != AGO_BF16 || gemm_packed_variant(M, K, N) == 0) return AGO_ERR_UNSUPPORTED;
+    if (dt != AGO_BF16 || !gemm_packed_ok(K, N)) return AGO_ERR_UNSUPPORTED;
     if (!fits31(M, K > N ? K : N, 1, 1) || !fits31(K, N, 1, 1)) return AGO_ERR_UNSUPPORTED;
     return AGO_OK;
 }

@@ -41,6 +41,14 @@ hipError_t scale(const void* x, void* y, long n, float alpha, bool bf16, hipStre
 hipError_t softmax_rows(const void* x, void* y, long rows, int cols, bool in_bf16, bool out_bf16,
                         hipStream_t s, int ld = 0);   // ld: elements per row of x and y (0 = cols), a multiple of 8; y's row tail is written as 0
 
+// bf16 products through direct-to-LDS rings (ago_gemm_dma.hpp)
+bool gemm_dma_ok(int K, int N, bool packed);                                     // divisibility only
+double gemm_dma_predict(int M, int K, int N, int siblings, int* tiling);         // microseconds; *tiling may be NULL
+hipError_t gemm_dma(const void* a, const void* w, bool packed, const float* bias, const void* res, void* c, int M, int K, int N,
+                    int act, hipStream_t s);                                     // res: row-major W only
+hipError_t gemm_dma_qkv(const void* x, const void* const w[3], const float* const b[3], void* const o[3], int B, int S, int K, int Hh,
+                        int D, bool head_major, hipStream_t s);                  // head_major: D % 8 == 0
+
 // fused subgraphs
 hipError_t fused_invres(const void* x, const void* w1, const float* b1, const void* wd, const float* bd,
                         const void* w2, const float* b2, void* y, int N, int H, int W, int Cin,
@@ -88,12 +96,15 @@ hipError_t ffn_reduce(const float* part, const float* b2, void* y, long MK2, int
                       long slice_stride = 0);
 // matmul -> activation -> matmul on weights packed into matrix-instruction fragments (pack_weight)
 bool fused_ffn_packed_ok(int M, int K, int F, int K2);
+// the chain as two products, the hidden tensor in the workspace: whether that is possible there and predicted faster than
+// fused_us (prof events bracket both)
+bool ffn_two_products_pay(int M, int K, int F, int K2, bool packed, size_t ws_bytes, double fused_us);
+hipError_t ffn_two_products(const void* x, const void* w1, const float* b1, const void* w2, const float* b2, void* y, int M, int K,
+                            int F, int K2, int act, bool packed, void* workspace, hipStream_t s);
 long fused_ffn_packed_rows(int M);
 int fused_ffn_packed_nsplit(int F);
 hipError_t pack_weight(const void* w, void* wp, int K, int N, hipStream_t s);
-int gemm_packed_variant(int M, int K, int N);     // 0: the shape fits no tiling of the packed product
-hipError_t gemm_packed(const void* a, const void* wp, const float* bias, void* c, int M, int K, int N, int act,
-                       hipStream_t s);
+bool gemm_packed_ok(int K, int N);                // sizes the packed product takes
 hipError_t fused_ffn_packed(const void* x, const void* w1p, const float* b1, const void* w2p, const float* b2,
                             void* y, int M, int K, int F, int K2, int act, void* workspace, hipStream_t s);
 int fused_ffn_num_cfgs();
