@@ -120,7 +120,8 @@ ago_status ago_fused_invres_noalloc(const void* x, const void* w1, const float* 
 /* Host-only: the tiling ago_fused_invres[_k] would launch for this shape (no GPU call).  The tile
  * is the candidate with the lowest predicted time of a cost model fitted to MI355X measurements
  * (the tile-size trade-off of Sec. III-B / Fig. 7a: re-computed halo against parallelism), or the
- * one set with ago_set_tile_config (tile candidate + 16 x channel-split option).  workspace_bytes: what
+ * one set with ago_set_tile_config (tile candidate + 16 x channel-split option; from 128 on the register-resident
+ * kernel's configurations, whose tile is what a workgroup's waves cover side by side).  workspace_bytes: what
  * the launch would be given (plans whose partials need more are not considered).  plan (host, 7 ints):
  * candidate index, tile rows, tile columns of output pixels, chunks of expanded channels one workgroup
  * walks, channels per chunk, LDS bytes, workgroups per tile (1 = no channel split).

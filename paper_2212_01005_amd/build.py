@@ -30,6 +30,15 @@ SOURCES = [
     "ago_gemm_dma_special.hip",
     "ago_conv.hip",
     "ago_fused_invres.hip",
+    "ago_invres_reg.hip",
+    "ago_invres_reg_b13.hip",
+    "ago_invres_reg_b15.hip",
+    "ago_invres_reg_b23.hip",
+    "ago_invres_reg_b25.hip",
+    "ago_invres_reg_f13.hip",
+    "ago_invres_reg_f15.hip",
+    "ago_invres_reg_f23.hip",
+    "ago_invres_reg_f25.hip",
     "ago_fused_conv_chain.hip",
     "ago_fused_ffn.hip",
     "ago_fused_ffn_stream.hip",

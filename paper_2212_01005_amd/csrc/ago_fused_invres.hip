@@ -30,6 +30,8 @@
 //           the image), stages 2-3 follow
 #include "ago_dev.hpp"
 #include "ago_launch.hpp"
+#include "ago_invres_reg.hpp"
+#include <string.h>
 #include <utility>
 
 namespace ago {
@@ -584,7 +586,8 @@ constexpr int kNumTiles = (int)(sizeof(kTileCand) / sizeof(kTileCand[0]));
 // workgroup may take; the chunks are then balanced to multiples of 32
 static const int kSplitCC[] = {0, 32, 64, 96, 128, 192, 256, 384};
 constexpr int kNumSplits = (int)(sizeof(kSplitCC) / sizeof(kSplitCC[0]));
-int fused_invres_num_cfgs() { return kNumTiles * kNumSplits; }
+constexpr int kTileCfgs = kNumTiles * kNumSplits;      // then the register-resident kernel's configurations
+int fused_invres_num_cfgs() { return kTileCfgs + invres_reg_num_cfgs(); }
 
 // Plan tile candidate `tile` with split option `so`.  Returns the LDS byte count, 0 when it cannot run
 // (does not fit, or the option does not apply: no reduction to split, a single chunk anyway).
@@ -612,10 +615,10 @@ static size_t choose_tile(InvresParams& p, bool bf16, int stride, int ksize, int
                           int* chosen, double* us) {
     int best = -1;
     double best_us = 0.0;
-    if (tile_cfg >= 0 && tile_cfg < fused_invres_num_cfgs()) {
+    if (tile_cfg >= 0 && tile_cfg < kTileCfgs) {
         best = tile_cfg;
     } else {
-        for (int c = 0; c < fused_invres_num_cfgs(); ++c) {
+        for (int c = 0; c < kTileCfgs; ++c) {
             const size_t sz = plan_candidate(p, bf16, stride, ksize, c % kNumTiles, c / kNumTiles);
             if (sz == 0 || invres_split_bytes(p) > ws_bytes) continue;
             const double t = predict_us(p, bf16, ksize, sz);
@@ -630,44 +633,98 @@ static size_t choose_tile(InvresParams& p, bool bf16, int stride, int ksize, int
     return smem;
 }
 
+// The two kernels of the block: the one above (workgroup tiles passing E and D through LDS; all modes), or the register-
+// resident one (the whole block only).
+struct InvresChoice {
+    bool reg;
+    int cfg;                 // configuration id
+    InvresParams p;          // !reg
+    InvresRegPlan q;         // reg
+    size_t smem;
+    double us;
+    size_t split_bytes;
+};
+static bool choose_invres(InvresChoice& c, int N, int H, int W, int Cin, int Cexp, int Cout, int stride, int ksize, bool bf16,
+                          int tile_cfg, int mode, size_t ws_bytes, bool lds_only = false) {
+    c.reg = false;
+    c.us = -1.0;
+    if (tile_cfg < kTileCfgs) {
+        c.p = InvresParams{};
+        c.p.mode = mode;
+        c.p.N = N; c.p.H = H; c.p.W = W; c.p.Cin = Cin; c.p.Cexp = Cexp; c.p.Cout = Cout;
+        c.p.OH = (H - 1) / stride + 1; c.p.OW = (W - 1) / stride + 1;
+        c.p.nsplit = 1;
+        c.smem = choose_tile(c.p, bf16, stride, ksize, tile_cfg, ws_bytes, &c.cfg, &c.us);
+        if (c.smem == 0) c.us = -1.0;
+        else c.split_bytes = invres_split_bytes(c.p);
+        // a shape of the specialisation table runs the specialised instantiation: measured at 0.6 x (one workgroup
+        // per tile) and 0.74 x (channel split: the reduction pass is unchanged) the general instantiation's time
+        if (c.smem && tile_cfg < 0 && ksize == 3) {
+            for (int id = 1; id < kNumInvresSpecs; ++id) {
+                if ((kInvresSpecs[id].bf16 != 0) != bf16 || kInvresSpecs[id].stride != stride) continue;
+                c.p.residual = kInvresSpecs[id].residual;
+                if (invres_matches_spec(c.p, id)) { c.us *= c.p.nsplit > 1 ? 0.74 : 0.6; break; }
+            }
+            c.p.residual = 0;
+        }
+    }
+    if (mode == 0 && (tile_cfg < 0 ? !lds_only : tile_cfg >= kTileCfgs)) {
+        InvresRegPlan q;
+        for (int r = 0; r < invres_reg_num_cfgs(); ++r) {
+            if (tile_cfg >= 0 && r != tile_cfg - kTileCfgs) continue;
+            if (!invres_reg_plan_cfg(q, r, N, H, W, Cin, Cexp, Cout, stride, ksize, bf16) || invres_reg_split_bytes(q) > ws_bytes) continue;
+            if (c.us >= 0.0 && c.us * (c.reg ? 1.0 : 0.97) <= q.us) continue;   // 3 %: the models' scatter
+            c.reg = true; c.cfg = kTileCfgs + r; c.q = q; c.us = q.us; c.smem = q.smem; c.split_bytes = invres_reg_split_bytes(q);
+        }
+    }
+    return c.us >= 0.0;
+}
+
 // Host-only query of the plan a launch would use with ws_bytes of workspace (no GPU call).
 // out: config, tile rows, tile columns, chunks per workgroup, chunk width, LDS bytes, workgroups per tile
 int fused_invres_plan(int N, int H, int W, int Cin, int Cexp, int Cout, int stride, int ksize, bool bf16,
                       int tile_cfg, int mode, size_t ws_bytes, int out[7], float* predicted_us) {
     if ((ksize != 3 && ksize != 5) || (stride != 1 && stride != 2)) return -1;
-    InvresParams p = {};
-    p.mode = mode;
-    p.N = N; p.H = H; p.W = W; p.Cin = Cin; p.Cexp = Cexp; p.Cout = Cout;
-    p.OH = (H - 1) / stride + 1; p.OW = (W - 1) / stride + 1;
-    int chosen = -1;
-    double us = 0.0;
-    const size_t smem = choose_tile(p, bf16, stride, ksize, tile_cfg, ws_bytes, &chosen, &us);
-    if (smem == 0) return -1;
-    out[0] = chosen; out[1] = p.TOH; out[2] = p.TOW; out[3] = p.nsplit > 1 ? 1 : p.nchunks; out[4] = p.CC;
-    out[5] = (int)smem; out[6] = p.nsplit;
-    // a shape of the specialisation table runs the specialised instantiation: measured at 0.6 x (one workgroup
-    // per tile) and 0.8 x (channel split: the reduction pass is unchanged) the general instantiation's time
-    if (tile_cfg < 0 && ksize == 3) {
-        for (int id = 1; id < kNumInvresSpecs; ++id) {
-            if ((kInvresSpecs[id].bf16 != 0) != bf16 || kInvresSpecs[id].stride != stride) continue;
-            p.residual = kInvresSpecs[id].residual;
-            if (invres_matches_spec(p, id)) { us *= p.nsplit > 1 ? 0.8 : 0.6; break; }
-        }
+    InvresChoice c;
+    if (!choose_invres(c, N, H, W, Cin, Cexp, Cout, stride, ksize, bf16, tile_cfg, mode, ws_bytes)) return -1;
+    const double us = c.us;
+    out[0] = c.cfg; out[5] = (int)c.smem;
+    if (c.reg) {
+        // the tile: what the waves of a workgroup cover side by side (strips of a row block first)
+        const InvresRegParams& r = c.q.p;
+        const int across = std::min(r.nwu, r.strips);
+        out[1] = r.rows * (r.nwu / across); out[2] = std::min(r.OW, across * ((r.OW + r.strips - 1) / r.strips)); out[3] = (r.cspan + r.csplit - 1) / r.csplit; out[4] = r.csplit;
+        out[6] = c.q.p.nsplit;
+        if (predicted_us) *predicted_us = (float)us;
+        return 0;
     }
+    const InvresParams& p = c.p;
+    out[1] = p.TOH; out[2] = p.TOW; out[3] = p.nsplit > 1 ? 1 : p.nchunks; out[4] = p.CC;
+    out[6] = p.nsplit;
     if (predicted_us) *predicted_us = (float)us;
     return 0;
 }
 
-// Workspace the preferred plan needs (0 when it does not split the expanded channels).
+// Workspace for the fastest plan of the LDS kernel (0 when it does not split the expanded channels), or for the one given.
+// The register-resident kernel is chosen within it, so that a caller's buffers keep their sizes; it splits less often.
 size_t fused_invres_workspace(int N, int H, int W, int Cin, int Cexp, int Cout, int stride, int ksize, bool bf16,
                               int tile_cfg, int mode) {
     if ((ksize != 3 && ksize != 5) || (stride != 1 && stride != 2)) return 0;
-    InvresParams p = {};
-    p.mode = mode;
-    p.N = N; p.H = H; p.W = W; p.Cin = Cin; p.Cexp = Cexp; p.Cout = Cout;
-    p.OH = (H - 1) / stride + 1; p.OW = (W - 1) / stride + 1;
-    if (choose_tile(p, bf16, stride, ksize, tile_cfg, ~(size_t)0, nullptr, nullptr) == 0) return 0;
-    return invres_split_bytes(p);
+    // a program that asks ahead of every launch (the graph executor does) would walk all candidates each time: the last
+    // few answers are kept per thread
+    struct Slot { int v[11]; size_t bytes; };
+    static thread_local Slot slots[32] = {};
+    static thread_local int next = 0;
+    const int key[11] = {N, H, W, Cin, Cexp, Cout, stride, ksize, bf16 ? 1 : 0, tile_cfg, mode};
+    for (const Slot& sl : slots)
+        if (memcmp(sl.v, key, sizeof(key)) == 0) return sl.bytes;                // N > 0: an empty slot never matches
+    InvresChoice c;
+    const bool fits = choose_invres(c, N, H, W, Cin, Cexp, Cout, stride, ksize, bf16, tile_cfg, mode, ~(size_t)0, true);
+    Slot& sl = slots[next];
+    next = (next + 1) % 32;
+    memcpy(sl.v, key, sizeof(key));
+    sl.bytes = fits ? c.split_bytes : 0;
+    return sl.bytes;
 }
 
 // Launch the shape-specialised instantiation whose geometry equals the run-time plan, if there is one.
@@ -704,11 +761,10 @@ hipError_t fused_invres(const void* x, const void* w1, const float* b1, const vo
     };
     struct PlanSlot {
         PlanKey key;
-        InvresParams p;
-        size_t smem;
+        InvresChoice c;
         bool valid;
     };
-    static thread_local PlanSlot plans[8] = {};
+    static thread_local PlanSlot plans[32] = {};
     static thread_local int next_slot = 0;
     const PlanKey key = {{N, H, W, Cin, Cexp, Cout, stride, ksize, bf16 ? 1 : 0, tile_cfg, mode}, workspace ? ws_bytes : 0};
     const PlanSlot* hit = nullptr;
@@ -718,23 +774,41 @@ hipError_t fused_invres(const void* x, const void* w1, const float* b1, const vo
         for (int q = 0; q < 11; ++q) same = same && sl.key.v[q] == key.v[q];
         if (same) { hit = &sl; break; }
     }
-    InvresParams p;
-    size_t smem;
-    if (hit) {
-        p = hit->p;
-        smem = hit->smem;
-    } else {
-        p = InvresParams{};
-        p.mode = mode;
-        p.N = N; p.H = H; p.W = W; p.Cin = Cin; p.Cexp = Cexp; p.Cout = Cout;
-        p.OH = (H - 1) / stride + 1; p.OW = (W - 1) / stride + 1;
-        p.nsplit = 1;
-        smem = choose_tile(p, bf16, stride, ksize, tile_cfg, key.ws, nullptr, nullptr);
-        if (smem == 0) return hipErrorInvalidValue;
+    if (!hit) {
         PlanSlot& sl = plans[next_slot];
-        next_slot = (next_slot + 1) % 8;
-        sl.key = key; sl.p = p; sl.smem = smem; sl.valid = true;
+        sl.valid = false;
+        if (!choose_invres(sl.c, N, H, W, Cin, Cexp, Cout, stride, ksize, bf16, tile_cfg, mode, key.ws)) return hipErrorInvalidValue;
+        next_slot = (next_slot + 1) % 32;
+        sl.key = key;
+        sl.valid = true;
+        hit = &sl;
     }
+    const long total = (long)N * ((H - 1) / stride + 1) * ((W - 1) / stride + 1) * Cout;
+    // sums the partial projections; b2 and the residual are left to this pass
+    auto reduce = [&](int nsplit) {
+        const unsigned rgrid = (unsigned)((total / 4 + 255) / 256);
+        if (bf16)
+            hipLaunchKernelGGL(invres_reduce_kernel<true>, dim3(rgrid), dim3(256), 0, s, static_cast<float*>(workspace), b2, residual ? x : nullptr, y,
+                               total, Cout, nsplit);
+        else
+            hipLaunchKernelGGL(invres_reduce_kernel<false>, dim3(rgrid), dim3(256), 0, s, static_cast<float*>(workspace), b2, residual ? x : nullptr, y,
+                               total, Cout, nsplit);
+        return hipGetLastError();
+    };
+    if (hit->c.reg) {
+        InvresRegPlan q = hit->c.q;
+        q.p.x = x; q.p.w1 = w1; q.p.b1 = b1; q.p.wd = wd; q.p.bd = bd; q.p.w2 = w2; q.p.b2 = b2; q.p.y = y;
+        q.p.part = static_cast<float*>(workspace);
+        q.p.residual = residual;
+        prof_start(0, s);
+        prof_shape(0, (unsigned)(q.groups * q.cogroups * q.p.nsplit), (unsigned)q.threads);
+        hipError_t e = invres_reg_launch(q, stride, ksize, bf16, s);
+        if (e == hipSuccess && q.p.nsplit > 1) e = reduce(q.p.nsplit);
+        prof_stop(0, s);
+        return e;
+    }
+    InvresParams p = hit->c.p;
+    const size_t smem = hit->c.smem;
     p.x = x; p.w1 = w1; p.b1 = b1; p.wd = wd; p.bd = bd; p.w2 = w2; p.b2 = b2; p.y = y;
     p.residual = residual;
     p.part = static_cast<float*>(workspace);
@@ -776,17 +850,9 @@ hipError_t fused_invres(const void* x, const void* w1, const float* b1, const vo
         prof_stop(0, s);
         return e;
     }
-    // sum the partial projections; b2 and the residual were left to this pass
-    const long total = (long)N * p.OH * p.OW * Cout;
-    const unsigned rgrid = (unsigned)((total / 4 + 255) / 256);
-    if (bf16)
-        hipLaunchKernelGGL(invres_reduce_kernel<true>, dim3(rgrid), dim3(256), 0, s, p.part, b2, residual ? x : nullptr, y,
-                           total, Cout, p.nsplit);
-    else
-        hipLaunchKernelGGL(invres_reduce_kernel<false>, dim3(rgrid), dim3(256), 0, s, p.part, b2, residual ? x : nullptr, y,
-                           total, Cout, p.nsplit);
+    e = reduce(p.nsplit);
     prof_stop(0, s);      // the event pair brackets the whole entry point, the reduction included
-    return hipGetLastError();
+    return e;
 }
 
 }  // namespace ago

@@ -1,0 +1,8 @@
+// Instantiations of ago_invres_reg.hpp: bf16, stride 2, depthwise 3 x 3.
+#include "ago_invres_reg.hpp"
+
+namespace ago {
+hipError_t invres_reg_b23(int ropt, int xr, int nco, const InvresRegParams& p, unsigned grid, unsigned threads, size_t smem, hipStream_t s) {
+    return invres_reg_run<true, 2, 3>(ropt, xr, nco, p, grid, threads, smem, s);
+}
+}  // namespace ago
