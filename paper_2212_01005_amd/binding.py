@@ -21,6 +21,8 @@ if not os.path.exists(LIB_PATH):
 
 lib = ctypes.CDLL(LIB_PATH)
 
+from . import _agocall   # noqa: E402  (native marshalling of the entry points, linked against the library loaded above)
+
 F32, BF16 = 0, 1
 ACT_NONE, ACT_RELU, ACT_RELU6, ACT_GELU_TANH = 0, 1, 2, 3
 OP_FUSED_INVRES, OP_FUSED_CONV_CHAIN, OP_FUSED_FFN, OP_FUSED_ATTN = 0, 1, 2, 3
@@ -299,12 +301,25 @@ def _want_bias(name, b, n):
 
 
 def _entry(marshal):
-    """Turn a marshalling function (tensors -> C function + argument tuple) into the entry point
-    wrapper; the marshalling step stays reachable for prepare()."""
-    def call(*a, **kw):
+    """Turn a marshalling function (tensors -> C function + argument tuple) into the entry point wrapper.  The native
+    form of the same checks and call (csrc/ago_pycall.cpp) goes first; arguments it does not take come back as None and
+    meet the Python form, which names what is wrong with them.  The marshalling step stays reachable for prepare()."""
+    code = marshal.__code__
+    native = _agocall.entry(marshal.__name__, code.co_varnames[:code.co_argcount])
+
+    def python_call(*a, **kw):
         fn, args = marshal(*a, **kw)
         _chk(fn(*args))
+
+    def native_call(*a, **kw):
+        st = native(*a, **kw)
+        if st is None:
+            python_call(*a, **kw)
+        elif st:
+            raise AgoError(st)
+    call = python_call if native is None else native_call
     call.marshal = marshal
+    call.native = native
     call.__name__ = marshal.__name__
     call.__doc__ = marshal.__doc__
     return call
@@ -313,7 +328,12 @@ def _entry(marshal):
 def prepare(entry, *a, **kw):
     """Marshal the arguments of an entry point once and return a zero-argument callable that
     launches it again with the same device pointers, sizes and stream (a serving loop calls the
-    same subgraph on the same buffers many times; only the C call remains per launch)."""
+    same subgraph on the same buffers many times; only the C call remains per launch).  The caller
+    keeps the tensors alive."""
+    if entry.native is not None:
+        launcher = entry.native.prepare(*a, **kw)
+        if launcher is not None:
+            return launcher
     fn, args = entry.marshal(*a, **kw)
 
     def run():
@@ -321,6 +341,12 @@ def prepare(entry, *a, **kw):
         if st:
             raise AgoError(st)
     return run
+
+
+def launch_sequence(launchers, held=None):
+    """One callable that issues a list of prepared launches in order, on the stream that is current when it is called;
+    `held` is kept alive with it."""
+    return _agocall.sequence(tuple(launchers), held)
 
 
 # ---- fused subgraphs ---------------------------------------------------------------

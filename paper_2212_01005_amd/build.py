@@ -1,4 +1,4 @@
-"""Build libago.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libago.so (HIP, gfx950 only) and the binding's native part in-tree with hipcc and g++.
 
     python -m paper_2212_01005_amd.build [--force]
 
@@ -15,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "obj")
 LIB = os.path.join(HERE, "libago.so")
+PYCALL = os.path.join(HERE, "_agocall.so")
 
 SOURCES = [
     "ago_host.cpp",
@@ -79,6 +80,24 @@ def _compile(src, force):
     return obj, True
 
 
+def _build_pycall(force):
+    """The binding's native marshalling: host code against the Python and torch headers, linked to libago.so."""
+    src = os.path.join(CSRC, "ago_pycall.cpp")
+    if not force and os.path.exists(PYCALL) and os.path.getmtime(PYCALL) >= max(os.path.getmtime(src), _deps_mtime()):
+        return
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    cmd += ["-isystem" + d for d in [sysconfig.get_paths()["include"], os.path.join(rocm, "include")] + include_paths()]
+    cmd += [src, "-o", PYCALL, "-L" + tlib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python",
+            "-L" + HERE, "-l:libago.so", "-Wl,-rpath,$ORIGIN"]
+    subprocess.check_call(cmd)
+
+
 def build(force: bool = False, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
@@ -87,6 +106,7 @@ def build(force: bool = False, jobs: int = 8) -> str:
     if force or any(c for _, c in results) or not os.path.exists(LIB):
         cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
         subprocess.check_call(cmd)
+    _build_pycall(force)
     return LIB
 
 

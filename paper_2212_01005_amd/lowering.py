@@ -167,6 +167,7 @@ class Executor:
         self.launches = 0
         self.pack_weights = bool(pack_weights) and g.dtype == "bf16"
         self.packed = {}                   # parameter name -> packed copy
+        self._compile()
 
     def _packed(self, name):
         """The packed copy of weight `name`, made on first use."""
@@ -182,152 +183,214 @@ class Executor:
 
     def _workspace(self, op, dims, dt):
         """Scratch the library asks for (cross-workgroup partial results), or None."""
-        nbytes = self.ago.workspace_bytes(op, [int(d) for d in dims], dt)
+        nbytes = self.ago.workspace_bytes(op, dims, dt)
         return self.torch.empty(max(nbytes, 16), dtype=self.torch.uint8, device=self.device) if nbytes else None
 
     def _bias_of(self, nodes, after):
-        """The bias that directly follows position `after` in a matched chain, or None."""
+        """Name of the bias that directly follows position `after` in a matched chain, or None."""
         if after + 1 < len(nodes) and nodes[after + 1].op == "bias":
-            return self.g.params[nodes[after + 1].attrs["b"]]
+            return nodes[after + 1].attrs["b"]
         return None
 
     def run(self, inputs):
-        g, ago, P, val = self.g, self.ago, self.g.params, {}
-        for i, n in enumerate(g.nodes):
-            if n.op == "input":
-                val[i] = inputs[n.attrs["name"]]
-        for kind, ids in self.plan:
-            nodes = [g.nodes[k] for k in ids]
-            x = val[nodes[0].inputs[0]]
-            self.launches += 1
-            if kind == "qkv":
-                ends = [k for k in ids if g.nodes[k].op == "to_heads"]
-                gemms = [k for k in ids if g.nodes[k].op == "gemm"]
-                biases = [next((P[g.nodes[b_].attrs["b"]] for b_ in ids if g.nodes[b_].op == "bias" and g.nodes[b_].inputs[0] == gm), None)
-                          for gm in gemms]
+        if self.g.params is not self._params:
+            self._compile()
+        val = {}
+        for i, name in self._inputs:
+            val[i] = inputs[name]
+        for step in self._steps:
+            entry, args = step(val)
+            entry(*args)
+        return {i: val[i] for i in self._results}
+
+    def _compile(self):
+        """The plan as one callable per launch: everything that follows from the graph (which parameters a launch takes,
+        strides, sizes of its output and workspace) is looked up here, once, so that a pass does little besides
+        allocating the outputs and calling the library.  Parameters are looked up by name at every pass."""
+        g, cons = self.g, self.g.consumers()
+        self._params = g.params
+        self._inputs = [(i, n.attrs["name"]) for i, n in enumerate(g.nodes) if n.op == "input"]
+        self._results = [i for i in range(len(g.nodes)) if not cons[i] and g.nodes[i].op != "input"]
+        self._steps = [self._step(kind, ids) for kind, ids in self.plan]
+
+    def _step(self, kind, ids):
+        """The launch as a function of the values so far: it allocates the outputs and returns the entry point and its
+        arguments (to_heads, a device copy, runs as ``_copy``)."""
+        g, ago, P = self.g, self.ago, self.g.params
+        nodes = [g.nodes[k] for k in ids]
+        src, dst = nodes[0].inputs[0], ids[-1]
+        dt = ago.BF16 if self.td == self.torch.bfloat16 else ago.F32
+        shape = [int(d) for d in self.shapes[src]]
+        pos = [k for k, n in enumerate(nodes) if n.op in COMPLEX]
+
+        def param(name):
+            return None if name is None else P[name]
+
+        if kind == "qkv":
+            ends = [k for k in ids if g.nodes[k].op == "to_heads"]
+            gemms = [k for k in ids if g.nodes[k].op == "gemm"]
+            weights = [g.nodes[gm].attrs["w"] for gm in gemms]
+            biases = [next((g.nodes[b_].attrs["b"] for b_ in ids if g.nodes[b_].op == "bias" and g.nodes[b_].inputs[0] == gm), None)
+                      for gm in gemms]
+            head_major = bool(g.nodes[ends[0]].attrs.get("head_major", True))
+
+            def step(val):
+                self.launches += 1
                 outs = [self._new(e) for e in ends]
-                ago.ago_fused_qkv(x, *(P[g.nodes[gm].attrs["w"]] for gm in gemms), *biases, *outs,
-                                  head_major=g.nodes[ends[0]].attrs.get("head_major", True))
+                args = (val[src], *(P[w] for w in weights), *(param(b_) for b_ in biases), *outs, head_major)
                 for e, o in zip(ends, outs):
                     val[e] = o
-                continue
-            out = self._new(ids[-1])
-            if kind == "invres":
-                pos = [k for k, n in enumerate(nodes) if n.op in COMPLEX]
-                w1, wd, w2 = (P[nodes[p].attrs["w"]] for p in pos)
-                residual = any(n.op == "add" for n in nodes)
-                stride = nodes[pos[1]].attrs.get("stride", 1)
-                fn = ago.ago_fused_invres if wd.shape[0] == 3 else ago.ago_fused_invres_k
-                dt = ago.BF16 if x.dtype == self.torch.bfloat16 else ago.F32
-                ws = self._workspace(ago.OP_FUSED_INVRES, list(x.shape) + [w1.shape[1], w2.shape[1], stride, wd.shape[0]], dt)
-                fn(x, w1, self._bias_of(nodes, pos[0]), wd, self._bias_of(nodes, pos[1]), w2,
-                   self._bias_of(nodes, pos[2]), out, stride, residual, ws)
-            elif kind == "pw_dw":
-                pos = [k for k, n in enumerate(nodes) if n.op in COMPLEX]
-                wd = P[nodes[pos[1]].attrs["w"]]
-                fn = ago.ago_fused_pw_dw if wd.shape[0] == 3 else ago.ago_fused_pw_dw_k
-                fn(x, P[nodes[pos[0]].attrs["w"]], self._bias_of(nodes, pos[0]), wd, self._bias_of(nodes, pos[1]), out,
-                   nodes[pos[1]].attrs.get("stride", 1))
-            elif kind == "dw_pw":
-                pos = [k for k, n in enumerate(nodes) if n.op in COMPLEX]
-                dt = ago.BF16 if x.dtype == self.torch.bfloat16 else ago.F32
-                w2 = P[nodes[pos[1]].attrs["w"]]
-                wd = P[nodes[pos[0]].attrs["w"]]
-                ws = self._workspace(ago.OP_FUSED_DW_PW,
-                                     list(x.shape) + [w2.shape[1], nodes[pos[0]].attrs.get("stride", 1), wd.shape[0]], dt)
-                fn = ago.ago_fused_dw_pw if wd.shape[0] == 3 else ago.ago_fused_dw_pw_k
-                fn(x, wd, self._bias_of(nodes, pos[0]), w2, self._bias_of(nodes, pos[1]), out,
-                   nodes[pos[0]].attrs.get("stride", 1), ws)
-            elif kind == "conv_chain":
-                pos = [k for k, n in enumerate(nodes) if n.op in COMPLEX]
-                ago.ago_fused_conv_chain(x, P[nodes[pos[0]].attrs["w"]], self._bias_of(nodes, pos[0]),
-                                         P[nodes[pos[1]].attrs["w"]], self._bias_of(nodes, pos[1]), out,
-                                         any(n.op == "add" for n in nodes))
-            elif kind in ("ffn", "ffn_epilogue"):
-                pos = [k for k, n in enumerate(nodes) if n.op in COMPLEX]
-                act = next(n.op for n in nodes if n.op in _ACT_OF)
-                w1, w2 = P[nodes[pos[0]].attrs["w"]], P[nodes[pos[1]].attrs["w"]]
-                dims = [x.shape[0], x.shape[1], w1.shape[1], w2.shape[1]]
-                n1, n2 = nodes[pos[0]].attrs["w"], nodes[pos[1]].attrs["w"]
-                if kind == "ffn":
-                    if self.pack_weights and ago.fused_ffn_packed_supported(*dims):
-                        ws = self._workspace(ago.OP_FUSED_FFN_PACKED, dims, ago.BF16)
-                        ago.ago_fused_ffn_packed(x, self._packed(n1), self._bias_of(nodes, pos[0]), self._packed(n2),
-                                                 self._bias_of(nodes, pos[1]), out, getattr(ago, _ACT_OF[act]), ws)
-                    else:
-                        ws = self._workspace(ago.OP_FUSED_FFN, dims, ago.BF16)
-                        ago.ago_fused_ffn(x, w1, self._bias_of(nodes, pos[0]), w2, self._bias_of(nodes, pos[1]), out,
-                                          getattr(ago, _ACT_OF[act]), ws)
-                else:                                  # two products with fused epilogues (two launches)
-                    self.launches += 1
-                    ws = self._workspace(ago.OP_UNFUSED_FFN, dims, ago.BF16)
-                    if (self.pack_weights and ago.gemm_packed_supported(dims[0], dims[1], dims[2])
-                            and ago.gemm_packed_supported(dims[0], dims[2], dims[3])):
-                        ago.ago_unfused_ffn_packed(x, self._packed(n1), self._bias_of(nodes, pos[0]), self._packed(n2),
-                                                   self._bias_of(nodes, pos[1]), out, getattr(ago, _ACT_OF[act]), ws)
-                    else:
-                        ago.ago_unfused_ffn(x, w1, self._bias_of(nodes, pos[0]), w2, self._bias_of(nodes, pos[1]), out,
-                                            getattr(ago, _ACT_OF[act]), True, ws)
-            elif kind == "attn":
-                k_t = val[nodes[0].inputs[1]]
-                v_t = val[[s for s in nodes[3].inputs if s not in ids][0]]
-                ago.ago_fused_attn(x, k_t, v_t, out, float(nodes[1].attrs["alpha"]))
-            else:
-                self._single(nodes[0], ids[0], val, out)
-            val[ids[-1]] = out
-        cons = g.consumers()
-        return {i: val[i] for i in range(len(g.nodes)) if not cons[i] and g.nodes[i].op != "input"}
+                return ago.ago_fused_qkv, args
+        elif kind == "invres":
+            w1, wd, w2 = (nodes[p].attrs["w"] for p in pos)
+            b1, bd, b2 = (self._bias_of(nodes, p) for p in pos)
+            residual = any(n.op == "add" for n in nodes)
+            stride = nodes[pos[1]].attrs.get("stride", 1)
+            ks = int(P[wd].shape[0])
+            fn = ago.ago_fused_invres if ks == 3 else ago.ago_fused_invres_k
+            dims = shape + [int(P[w1].shape[1]), int(P[w2].shape[1]), int(stride), ks]
+
+            def step(val):
+                self.launches += 1
+                out = val[dst] = self._new(dst)
+                return fn, (val[src], P[w1], param(b1), P[wd], param(bd), P[w2], param(b2), out, stride, residual,
+                            self._workspace(ago.OP_FUSED_INVRES, dims, dt))
+        elif kind == "pw_dw":
+            w1, wd = (nodes[p].attrs["w"] for p in pos)
+            b1, bd = (self._bias_of(nodes, p) for p in pos)
+            stride = nodes[pos[1]].attrs.get("stride", 1)
+            fn = ago.ago_fused_pw_dw if P[wd].shape[0] == 3 else ago.ago_fused_pw_dw_k
+
+            def step(val):
+                self.launches += 1
+                out = val[dst] = self._new(dst)
+                return fn, (val[src], P[w1], param(b1), P[wd], param(bd), out, stride)
+        elif kind == "dw_pw":
+            wd, w2 = (nodes[p].attrs["w"] for p in pos)
+            bd, b2 = (self._bias_of(nodes, p) for p in pos)
+            stride = nodes[pos[0]].attrs.get("stride", 1)
+            ks = int(P[wd].shape[0])
+            fn = ago.ago_fused_dw_pw if ks == 3 else ago.ago_fused_dw_pw_k
+            dims = shape + [int(P[w2].shape[1]), int(stride), ks]
+
+            def step(val):
+                self.launches += 1
+                out = val[dst] = self._new(dst)
+                return fn, (val[src], P[wd], param(bd), P[w2], param(b2), out, stride, self._workspace(ago.OP_FUSED_DW_PW, dims, dt))
+        elif kind == "conv_chain":
+            wa, wb = (nodes[p].attrs["w"] for p in pos)
+            ba, bb = (self._bias_of(nodes, p) for p in pos)
+            residual = any(n.op == "add" for n in nodes)
+
+            def step(val):
+                self.launches += 1
+                out = val[dst] = self._new(dst)
+                return ago.ago_fused_conv_chain, (val[src], P[wa], param(ba), P[wb], param(bb), out, residual)
+        elif kind in ("ffn", "ffn_epilogue"):
+            n1, n2 = (nodes[p].attrs["w"] for p in pos)
+            b1, b2 = (self._bias_of(nodes, p) for p in pos)
+            act = getattr(ago, _ACT_OF[next(n.op for n in nodes if n.op in _ACT_OF)])
+            dims = [shape[0], shape[1], int(P[n1].shape[1]), int(P[n2].shape[1])]
+            if kind == "ffn":
+                packed = self.pack_weights and ago.fused_ffn_packed_supported(*dims)
+                op, fn = ((ago.OP_FUSED_FFN_PACKED, ago.ago_fused_ffn_packed) if packed else (ago.OP_FUSED_FFN, ago.ago_fused_ffn))
+                tail = ()
+            else:                                      # two products with fused epilogues (two launches)
+                packed = (self.pack_weights and ago.gemm_packed_supported(dims[0], dims[1], dims[2])
+                          and ago.gemm_packed_supported(dims[0], dims[2], dims[3]))
+                op, fn = ago.OP_UNFUSED_FFN, ago.ago_unfused_ffn_packed if packed else ago.ago_unfused_ffn
+                tail = () if packed else (True,)
+            weight = self._packed if packed else P.__getitem__
+            count = 1 if kind == "ffn" else 2
+
+            def step(val):
+                self.launches += count
+                out = val[dst] = self._new(dst)
+                return fn, (val[src], weight(n1), param(b1), weight(n2), param(b2), out, act, *tail, self._workspace(op, dims, ago.BF16))
+        elif kind == "attn":
+            k_src, v_src = nodes[0].inputs[1], [s for s in nodes[3].inputs if s not in ids][0]
+            alpha = float(nodes[1].attrs["alpha"])
+
+            def step(val):
+                self.launches += 1
+                out = val[dst] = self._new(dst)
+                return ago.ago_fused_attn, (val[src], val[k_src], val[v_src], out, alpha)
+        else:
+            def step(val):
+                self.launches += 1
+                out = val[dst] = self._new(dst)
+                return self._single(nodes[0], val, out)
+        return step
 
     def capture(self, example_inputs):
-        """Record one pass of the plan into a HIP graph: a plan of small kernels (a network at batch 1 is a
-        few microseconds per launch) is bound by launch overhead, and a replay issues all of them with one call.
-        Returns (replay, inputs, outputs): copy new data into ``inputs[name]`` (static buffers), call
-        ``replay()``, read ``outputs`` (the same dict ``run`` returns, static buffers as well).  One eager
-        pass runs first so that one-time set-up (function attributes) stays out of the capture."""
+        """Record one pass of the plan for replay: a plan of small kernels (a network at batch 1 is a few microseconds
+        per launch) is bound by what issues them.  Returns (replay, inputs, outputs): copy new data into
+        ``inputs[name]`` (static buffers), call ``replay()``, read ``outputs`` (the same dict ``run`` returns, static
+        buffers as well).  The recording holds everything it uses.  One eager pass runs first so that one-time set-up
+        (function attributes, packed weights) stays out of it.
+
+        A plan of library calls only becomes a list of marshalled calls that one native call issues on the current
+        stream; otherwise the pass is recorded into a HIP graph.  The list is the faster of the two: 22 kernels of the
+        16-block network body take 110 us as a list and 126 us as a graph (a replayed graph starts later and leaves
+        longer gaps between its nodes)."""
         torch = self.torch
         static_in = {k: v.clone() for k, v in example_inputs.items()}
         self.run(static_in)
         torch.cuda.synchronize()
+        val = {i: static_in[name] for i, name in self._inputs}
+        launchers, held = [], [static_in]
+        for step in self._steps:
+            entry, args = step(val)
+            launcher = entry.native.prepare(*args) if getattr(entry, "native", None) is not None else None
+            if launcher is None:
+                break
+            launcher()
+            launchers.append(launcher)
+            held.append(args)
+        else:
+            return self.ago.launch_sequence(launchers, held), static_in, {i: val[i] for i in self._results}
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
             static_out = self.run(static_in)
         self._graph = graph                # keeps the graph (and its memory pool) alive with the executor
         return graph.replay, static_in, static_out
 
-    def _single(self, n, i, val, out):
+    def _copy(self, src, out):
+        out.copy_(src)                     # a device copy, no arithmetic
+
+    def _single(self, n, val, out):
         ago, P = self.ago, self.g.params
         a = val[n.inputs[0]]
         if n.op == "conv1x1":
-            ago.ago_conv1x1(a, P[n.attrs["w"]], None, None, out)
+            return ago.ago_conv1x1, (a, P[n.attrs["w"]], None, None, out)
         elif n.op == "gemm":
             w = P[n.attrs["w"]]
             if self.pack_weights and ago.gemm_packed_supported(a.shape[0], w.shape[0], w.shape[1]):
-                ago.ago_gemm_packed(a, self._packed(n.attrs["w"]), None, out)
+                return ago.ago_gemm_packed, (a, self._packed(n.attrs["w"]), None, out)
             else:
-                ago.ago_gemm(a, w, None, None, out)
+                return ago.ago_gemm, (a, w, None, None, out)
         elif n.op == "dwconv":
             if P[n.attrs["w"]].shape[0] != 3:
                 raise NotImplementedError("un-fused depthwise kernels other than 3x3")
-            ago.ago_dwconv3x3(a, P[n.attrs["w"]], None, out, n.attrs.get("stride", 1))
+            return ago.ago_dwconv3x3, (a, P[n.attrs["w"]], None, out, n.attrs.get("stride", 1))
         elif n.op == "conv3x3":
-            ago.ago_conv3x3(a, P[n.attrs["w"]], None, None, out)
+            return ago.ago_conv3x3, (a, P[n.attrs["w"]], None, None, out)
         elif n.op == "bias":
-            ago.ago_bias_act(a, P[n.attrs["b"]], out)
+            return ago.ago_bias_act, (a, P[n.attrs["b"]], out)
         elif n.op in _ACT_OF:
-            ago.ago_bias_act(a, None, out, getattr(ago, _ACT_OF[n.op]))
+            return ago.ago_bias_act, (a, None, out, getattr(ago, _ACT_OF[n.op]))
         elif n.op == "add":
-            ago.ago_add_act(a, val[n.inputs[1]], out)
+            return ago.ago_add_act, (a, val[n.inputs[1]], out)
         elif n.op == "scale":
-            ago.ago_scale(a, out, float(n.attrs["alpha"]))
+            return ago.ago_scale, (a, out, float(n.attrs["alpha"]))
         elif n.op == "softmax":
-            ago.ago_softmax_rows(a, out)
+            return ago.ago_softmax_rows, (a, out)
         elif n.op == "to_heads":
             b_, hh = n.attrs["batch"], n.attrs["heads"]
             v4 = a.view(b_, a.shape[0] // b_, hh, a.shape[1] // hh)
-            out.copy_(v4.permute(0, 2, 1, 3) if n.attrs.get("head_major", True) else v4)   # a device copy, no arithmetic
+            return self._copy, (v4.permute(0, 2, 1, 3) if n.attrs.get("head_major", True) else v4, out)
         elif n.op == "bmm_nt":
-            ago.ago_bmm_nt(a, val[n.inputs[1]], out)
+            return ago.ago_bmm_nt, (a, val[n.inputs[1]], out)
         elif n.op == "bmm_nn":
-            ago.ago_bmm_nn(a, val[n.inputs[1]], out)
-        else:
-            raise ValueError(n.op)
+            return ago.ago_bmm_nn, (a, val[n.inputs[1]], out)
+        raise ValueError(n.op)
