@@ -328,9 +328,8 @@ def _entry(marshal):
 def prepare(entry, *a, **kw):
     """Marshal the arguments of an entry point once and return a zero-argument callable that
     launches it again with the same device pointers, sizes and stream (a serving loop calls the
-    same subgraph on the same buffers many times; only the C call remains per launch).  The
-    callable keeps the tensors alive: a launch on memory that the allocator has handed out again would read
-    another tensor's values."""
+    same subgraph on the same buffers many times; only the C call remains per launch).  The caller
+    keeps the tensors alive."""
     if entry.native is not None:
         launcher = entry.native.prepare(*a, **kw)
         if launcher is not None:
@@ -341,7 +340,6 @@ def prepare(entry, *a, **kw):
         st = fn(*args)
         if st:
             raise AgoError(st)
-    run.held = (a, kw)
     return run
 
 

@@ -506,7 +506,6 @@ struct Launcher {
     PyObject_HEAD
     vectorcallfunc vectorcall;
     Launch launch;
-    PyObject* held;               // the arguments: their memory is read again at every launch
 };
 
 int run_released(const Launch& l) {
@@ -604,7 +603,6 @@ void entry_dealloc(PyObject* self) {
     Py_DECREF(tp);
 }
 void launcher_dealloc(PyObject* self) {
-    Py_XDECREF(((Launcher*)self)->held);
     PyTypeObject* tp = Py_TYPE(self);
     tp->tp_free(self);
     Py_DECREF(tp);
@@ -628,13 +626,6 @@ PyObject* entry_prepare(PyObject* self, PyObject* const* args, Py_ssize_t n, PyO
     if (!la) return nullptr;
     la->vectorcall = launcher_call;
     la->launch = l;
-    const Py_ssize_t total = n + (kwnames ? PyTuple_GET_SIZE(kwnames) : 0);
-    la->held = PyTuple_New(total);
-    if (!la->held) { Py_DECREF(la); return nullptr; }
-    for (Py_ssize_t i = 0; i < total; ++i) {
-        Py_INCREF(args[i]);
-        PyTuple_SET_ITEM(la->held, i, args[i]);
-    }
     return (PyObject*)la;
 }
 

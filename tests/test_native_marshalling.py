@@ -43,24 +43,3 @@ def test_native_calls_equal_python_calls(case):
         entry(*put(ys[0][..., :-1]))
     with pytest.raises(ValueError):
         entry(*put(ys[0].double()))
-
-
-@pytest.mark.gpu
-@pytest.mark.parametrize("native", [True, False])
-def test_prepared_launch_keeps_its_tensors(native, monkeypatch):
-    import weakref
-    import torch
-    from paper_2212_01005_amd import binding as ago
-    entry = ago.ago_add_act
-    if not native:
-        monkeypatch.setattr(entry, "native", None)
-    y = torch.empty(64, 32, device="cuda")
-    tensors = [torch.full((64, 32), v, device="cuda") for v in (1.0, 2.0)]
-    refs = [weakref.ref(t) for t in tensors]
-    launcher = ago.prepare(entry, *tensors, y=y)
-    del tensors
-    others = [torch.full((64, 32), 5.0, device="cuda") for _ in range(4)]     # would take the freed blocks
-    launcher()
-    assert torch.equal(y, torch.full_like(y, 3.0)) and len(others) == 4
-    del launcher
-    assert all(r() is None for r in refs)
