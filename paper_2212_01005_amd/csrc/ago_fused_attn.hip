@@ -60,12 +60,12 @@ __device__ __forceinline__ bf16x8 lds_read_vt(const lds_byte* p) {
 // NP: 64-column planes of the head dimension (D = 64 NP).  A K or V block is stored plane by plane,
 // [plane][128 keys][64], each plane with the layout described at the top, so every fragment address is
 // the D = 64 one plus a plane offset.
-template <int NQT, int NSTG, int BIAS /* 0 none, 1 rows by 16-byte loads, 2 element by element */, int NP = 1>
+template <int NQT, int NSTG, int BIAS /* 0 none, 1 rows that start on a dword, 2 rows that may not */, int NP = 1>
 __global__ __launch_bounds__((2 * NQT + 2) * 64)
-__attribute__((amdgpu_waves_per_eu(NP == 2 || BIAS == 2 ? 2 : (BIAS == 1 ? 4 : 3), 4))) void fused_attn_kernel(
+__attribute__((amdgpu_waves_per_eu(NP == 2 ? 2 : (BIAS ? 4 : 3), 4))) void fused_attn_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, int S, int heads, int qblocks, int Hh, long stride_b, long stride_h, long stride_s,
-    float c /* scale * log2(e) */, const bf16_t* __restrict__ Bias, long bias_sb, long bias_sh) {
+    float c /* scale * log2(e); with a bias: scale */, const bf16_t* __restrict__ Bias, long bias_sb, long bias_sh) {
     constexpr bool HAS_BIAS = BIAS != 0;
     constexpr int kBlockB = NP * kPlaneB;
     static_assert(NP == 1 || NSTG == 2, "two planes: two buffers");
@@ -160,52 +160,47 @@ __attribute__((amdgpu_waves_per_eu(NP == 2 || BIAS == 2 ? 2 : (BIAS == 1 ? 4 : 3
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
     float m = -INFINITY, l = 0.f;     // running max of scaled scores, running (per-half) sum
-    // with a bias the scores are rescaled (and biased) once, ahead of the max; without, the scale rides
-    // in the exponent's multiply-add
-    const float ce = HAS_BIAS ? 1.f : c;
-    const bf16_t* brow = nullptr;
-    if constexpr (HAS_BIAS)
-        brow = Bias + (long)(head / Hh) * bias_sb + (long)(head % Hh) * bias_sh + (long)min(q_row, S - 1) * S;
+    // with a bias the scores are scaled and biased by one multiply-add ahead of the max and log2(e) rides in the
+    // exponent's; without, the whole scale does
+    const float ce = HAS_BIAS ? 1.4426950408889634f : c;
 
     // Bias values of the lane's query row: register group gq of key tile kt covers the 4 consecutive
-    // keys 4 h + 8 gq (+ 32 kt + 64 kh).  BIAS == 1 (S % 8 == 0, 16-byte aligned rows): lane (j, h) loads
-    // the 8 keys 16 p + 8 h .. + 7 in one 16-byte access; its low half belongs to the h = 0 lane and its
-    // high half to the h = 1 lane, so one swap of 32-lane halves per register pair (done when the values
-    // are used) hands every lane its groups 2 p and 2 p + 1.  A chunk beyond S is clamped to the row's
-    // last chunk (those keys are masked).  The loads are issued ahead of the block's first product; holding
-    // them a whole iteration ahead would cost the 16 registers that separate 4 waves per SIMD from 3.
-    uint4 bw[2][2];
+    // keys 4 h + 8 gq (+ 32 kt + 64 kh).  Lane (j, h) loads the 8 keys 16 p + 8 h .. + 7 in one 16-byte access;
+    // its low half belongs to the h = 0 lane and its high half to the h = 1 lane, so one swap of 32-lane halves
+    // per register pair (done when the values are used) hands every lane its groups 2 p and 2 p + 1.  The
+    // buffer's range stands for bounds checks: what lies beyond the matrix reads as 0, what lies beyond a row is
+    // the next row's, and both are keys from S on, which are masked.  A load costs twice as much off a dword
+    // boundary, so rows that may start between two (odd S) are read from the dword below and moved up; their
+    // eighth value is in the next piece of the row, which the other half of the wave, or this lane's next load,
+    // holds.  The next block's loads are issued ahead of this block's second product, where the scores' registers
+    // are free; earlier they would cost the 16 registers that separate 4 waves per SIMD from 3.  The vector ALUs bound a block, so a
+    // score spends two instructions on its bias (unpack, multiply-add).
+    // Measured on 4 x 12 heads, D = 64, one matrix per batch (us; before: three instructions per score, loads at the block's
+    // start, element by element where S % 8 != 0): S = 1000: 36.5 -> 30.2, S = 1001: 81.8 -> 33.0; without a bias 23.3.
+    const int row0 = qblk * (32 * NQT);
+    const bf16_t* b0 = HAS_BIAS ? Bias + (long)(head / Hh) * bias_sb + (long)(head % Hh) * bias_sh + (long)row0 * S : nullptr;
+    const int skew = (int)(reinterpret_cast<uintptr_t>(b0) & 2);
+    const auto bbuf = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(b0) & ~(uintptr_t)3), 0,
+                                                        (min(S - row0, 32 * NQT) * S * 2 + skew + 3) & ~3, 0x00020000);   // the last value's dword included
+    const int at = (min(q_row, S - 1) - row0) * S * 2 + skew + (64 * kh + 8 * h) * 2;
+    const int boff = at & ~3;              // the lane's first byte of a block's 128 keys
+    const unsigned bshift = (at & 2) * 8;  // bits by which its row starts after that
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 bw[4];                           // 16 keys each: key tile i / 2, register groups 2 (i & 1) and + 1
+    unsigned btail = 0;
     auto load_bias = [&](int blk) {
-        const int key_wave = blk * kKB + 64 * kh;
-        if constexpr (BIAS == 1) {
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int pr = 0; pr < 2; ++pr)
-                    bw[kt][pr] = ld_u4(brow + min(key_wave + kt * 32 + 16 * pr + 8 * h, S - 8));
-        } else {
-            const unsigned short* be = reinterpret_cast<const unsigned short*>(brow);
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int pr = 0; pr < 2; ++pr) {
-                    unsigned e8[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int key = key_wave + 4 * h + kt * 32 + 16 * pr + 8 * (e >> 2) + (e & 3);
-                        e8[e] = be[min(key, S - 1)];
-                    }
-                    bw[kt][pr] = make_uint4(e8[0] | (e8[1] << 16), e8[2] | (e8[3] << 16), e8[4] | (e8[5] << 16),
-                                            e8[6] | (e8[7] << 16));
-                }
-        }
+        for (int i = 0; i < 4; ++i) bw[i] = __builtin_amdgcn_raw_buffer_load_b128(bbuf, boff + 32 * i, blk * (kKB * 2), 0);
+        if constexpr (BIAS == 2) btail = __builtin_amdgcn_raw_buffer_load_b32(bbuf, boff + 112, blk * (kKB * 2), 0);
     };
+    constexpr bool AHEAD = BIAS == 1 || NP == 2;      // the odd rows' extra registers would spill at 128
+    if constexpr (HAS_BIAS && AHEAD) load_bias(0);
     __builtin_amdgcn_s_barrier();     // block 0 is in LDS
     for (int blk = 0; blk < nblk; ++blk) {
         const lds_byte* kb = smem + (blk % NSTG) * 2 * kBlockB;
         const lds_byte* vb = kb + kBlockB;
 
-        if constexpr (HAS_BIAS) load_bias(blk);     // in flight across the first product
+        if constexpr (HAS_BIAS && !AHEAD) load_bias(blk);              // in flight across the first product
 
         f32x16 sc[2];
 #pragma unroll
@@ -220,25 +215,28 @@ __attribute__((amdgpu_waves_per_eu(NP == 2 || BIAS == 2 ? 2 : (BIAS == 1 ? 4 : 3
                                 qf[ks], sc[kt]);
 
         if constexpr (HAS_BIAS) {
-            constexpr float kLog2e = 1.4426950408889634f;
+            if constexpr (BIAS == 2) {
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int pr = 0; pr < 2; ++pr) {
-                    uint4 w = bw[kt][pr];
-                    if constexpr (BIAS == 1) {
-                        const auto s0 = __builtin_amdgcn_permlane32_swap(w.x, w.z, false, false);
-                        const auto s1 = __builtin_amdgcn_permlane32_swap(w.y, w.w, false, false);
-                        w = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-                    }
-                    const unsigned raw[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int r = 8 * pr + 2 * e;                  // registers r, r + 1 of key tile kt
-                        sc[kt][r] = fmaf(sc[kt][r], c, __uint_as_float(raw[e] << 16) * kLog2e);
-                        sc[kt][r + 1] = fmaf(sc[kt][r + 1], c, __uint_as_float(raw[e] & 0xffff0000u) * kLog2e);
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    // the dword after these four: h = 0: the other half's first of this load, h = 1: the other half's first of the next
+                    const auto nx = __builtin_amdgcn_permlane32_swap(bw[i][0], i < 3 ? bw[i + 1][0] : 0u, false, false);
+                    const unsigned w4 = h == 0 ? nx[1] : i < 3 ? nx[0] : btail;
+                    bw[i] = u32x4{__builtin_amdgcn_alignbit(bw[i][1], bw[i][0], bshift), __builtin_amdgcn_alignbit(bw[i][2], bw[i][1], bshift),
+                                  __builtin_amdgcn_alignbit(bw[i][3], bw[i][2], bshift), __builtin_amdgcn_alignbit(w4, bw[i][3], bshift)};
                 }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const auto s0 = __builtin_amdgcn_permlane32_swap(bw[i][0], bw[i][2], false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(bw[i][1], bw[i][3], false, false);
+                const unsigned raw[4] = {s0[0], s1[0], s0[1], s1[1]};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 8 * (i & 1) + 2 * e;                 // registers r, r + 1 of key tile i / 2
+                    sc[i >> 1][r] = fmaf(sc[i >> 1][r], c, __uint_as_float(raw[e] << 16));
+                    sc[i >> 1][r + 1] = fmaf(sc[i >> 1][r + 1], c, __uint_as_float(raw[e] & 0xffff0000u));
+                }
+            }
         }
         // mask keys beyond S (only a block that straddles S needs it; the test is wave-uniform)
         if ((blk + 1) * kKB > S) {
@@ -289,6 +287,7 @@ __attribute__((amdgpu_waves_per_eu(NP == 2 || BIAS == 2 ? 2 : (BIAS == 1 ? 4 : 3
                     l += pv;
                     pf[kt][u][e] = (bf16_t)pv;
                 }
+        if constexpr (HAS_BIAS && AHEAD) load_bias(min(blk + 1, nblk - 1));      // the scores' registers are free: in flight across both products
         // the lane's two V^T base addresses of this block, once: the 8 NP fragment addresses are these plus constants
         const lds_byte* vbase[2] = {vb + voff[0], vb + voff[1]};
 #pragma unroll
@@ -365,7 +364,7 @@ static hipError_t launch_attn(const void* q, const void* k, const void* v, void*
     prof_shape(3, grid.x, (2 * NQT + 2) * 64);
     hipLaunchKernelGGL(kern, grid, dim3((2 * NQT + 2) * 64), smem, s, (const bf16_t*)q, (const bf16_t*)k,
                        (const bf16_t*)v, (bf16_t*)o, S, heads, qblocks, Hh, stride_b, stride_h, stride_s,
-                       scale * 1.4426950408889634f, (const bf16_t*)bias.ptr, bias.sb, bias.sh);
+                       BIAS ? scale : scale * 1.4426950408889634f, (const bf16_t*)bias.ptr, bias.sb, bias.sh);
     prof_stop(3, s);
     return hipGetLastError();
 }
@@ -401,27 +400,26 @@ hipError_t fused_attn_bias(const void* q, const void* k, const void* v, const vo
                            int S, long bias_sb, long bias_sh, float scale, int tile_cfg, hipStream_t s, int D) {
     const long stride_b = (long)Hh * S * D, stride_h = (long)S * D, stride_s = D;
     const AttnBias bs{bias, bias_sb, bias_sh};
-    // Two LDS buffers throughout (the third costs the registers that the bias values need); the
-    // element-by-element variant needs more registers still and runs configuration 3 as configuration 1.
+    // every row starts on a dword: 16-byte loads as they are
+    const bool dwords = S % 2 == 0 && bias_sb % 2 == 0 && bias_sh % 2 == 0 && reinterpret_cast<uintptr_t>(bias) % 4 == 0;
+    if (D == 128) {
+        if (dwords) return launch_attn<3, 2, 1, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs);
+        return launch_attn<3, 2, 2, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs);
+    }
+    if (D != 64) return hipErrorInvalidValue;
     if (tile_cfg < 0) {
         AttnPlan plan;
         tile_cfg = plan_attn(B, Hh, S, 64, -1, &plan) ? plan.cfg : 0;
     }
-    // 16-byte loads of 8 bias values need every row start 16-byte aligned
-    const bool vec = S % 8 == 0 && bias_sb % 8 == 0 && bias_sh % 8 == 0 && reinterpret_cast<uintptr_t>(bias) % 16 == 0;
-    if (D == 128) {
-        if (vec) return launch_attn<3, 2, 1, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs);
-        return launch_attn<3, 2, 2, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs);
-    }
-    if (D != 64) return hipErrorInvalidValue;
-#define AGO_ATTN_BIAS_CASE(NQT, NQT_E)                                                                        \
-    return vec ? launch_attn<NQT, 2, 1>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs)     \
-               : launch_attn<NQT_E, 2, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs)
+    // two LDS buffers throughout (the third costs the registers that the bias values need)
+#define AGO_ATTN_BIAS_CASE(NQT)                                                                               \
+    return dwords ? launch_attn<NQT, 2, 1>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs)   \
+                  : launch_attn<NQT, 2, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs)
     switch (tile_cfg) {
-        case 1: AGO_ATTN_BIAS_CASE(4, 4);
-        case 2: AGO_ATTN_BIAS_CASE(2, 2);
-        case 3: AGO_ATTN_BIAS_CASE(6, 4);
-        default: AGO_ATTN_BIAS_CASE(3, 3);
+        case 1: AGO_ATTN_BIAS_CASE(4);
+        case 2: AGO_ATTN_BIAS_CASE(2);
+        case 3: AGO_ATTN_BIAS_CASE(6);
+        default: AGO_ATTN_BIAS_CASE(3);
     }
 #undef AGO_ATTN_BIAS_CASE
 }
