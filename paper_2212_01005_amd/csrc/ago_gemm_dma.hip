@@ -22,6 +22,12 @@ constexpr TilingModel kModel[kGemmTilings] = {
     {32, 32, {1.801f, 1.829f, 0.0193f, 0.0f, 0.0359f}},
     {32, 64, {1.531f, 2.212f, 0.04f, 0.0f, 0.0256f}},
 };
+// threads of a workgroup
+#define AGO_GEMM_SHARED(ID, BM, BN, WM, WN, NST) WM * WN * 64,
+#define AGO_GEMM_SPLIT(ID, BM, BN, WAVES, NST) WAVES * 64,
+constexpr int kThreads[kGemmTilings] = {AGO_GEMM_TILINGS(AGO_GEMM_SHARED, AGO_GEMM_SPLIT)};
+#undef AGO_GEMM_SHARED
+#undef AGO_GEMM_SPLIT
 }  // namespace
 
 double gemm_dma_predict(int M, int K, int N, int siblings, int* tiling) {
@@ -78,7 +84,11 @@ bool ffn_two_products_pay(int M, int K, int F, int K2, bool packed, size_t ws_by
 
 hipError_t ffn_two_products(const void* x, const void* w1, const float* b1, const void* w2, const float* b2, void* y, int M, int K,
                             int F, int K2, int act, bool packed, void* workspace, hipStream_t s) {
-    prof_start(2, s);
+    int tiling = 0;
+    gemm_dma_predict(M, K, F, 1, &tiling);
+    const TilingModel& m = kModel[tiling];
+    prof_start(2, s);      // no split: either product is a part of the chain only
+    prof_shape(2, (unsigned)((((long)M + m.bm - 1) / m.bm) * (((long)F + m.bn - 1) / m.bn)), (unsigned)kThreads[tiling]);
     hipError_t e = gemm_dma(x, w1, packed, b1, nullptr, workspace, M, K, F, act, s);
     if (e == hipSuccess) e = gemm_dma(workspace, w2, packed, b2, nullptr, y, M, F, K2, kNone, s);
     prof_stop(2, s);

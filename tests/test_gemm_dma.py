@@ -80,3 +80,19 @@ def test_sibling_projections(oracle, b, s, k, hh, d, head_major):
     for o, wi, bi in zip(out, w, bias):
         ref = oracle.bias(oracle.gemm(x, wi), bi).reshape(b, s, hh, d)
         _check(o, ref.transpose(0, 2, 1, 3) if head_major else ref)
+
+
+@pytest.mark.parametrize("m", [128, 2048])
+def test_two_products_report_their_launch(m):
+    import torch
+    from paper_2212_01005_amd import binding as ago
+    k, f = 768, 3072
+    x, w1, w2 = (torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((m, k), (k, f), (f, k)))
+    b1, b2 = torch.zeros(f, device="cuda"), torch.zeros(k, device="cuda")
+    y, ws = torch.empty_like(x), torch.empty(ago.workspace_bytes(ago.OP_FUSED_FFN, [m, k, f, k], ago.BF16), dtype=torch.uint8, device="cuda")
+    ago.bench_empty_kernel(1, 64)
+    ago.ago_fused_ffn(x, w1, b1, w2, b2, y, ago.ACT_GELU_TANH, ws)
+    torch.cuda.synchronize()
+    grid, block = ago.profile_last_launch(ago.OP_FUSED_FFN)
+    # tiles of 32 x 32 up to 128 x 256 of the first product
+    assert block in (256, 512) and m * f // (128 * 256) <= grid <= m * f // (32 * 32)
