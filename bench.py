@@ -30,12 +30,10 @@ sys.path.insert(0, ROOT)
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 PEAK_F32_TFLOPS = 157.3       # fp32 MFMA / vector
 PEAK_HBM_GBS = 8000.0
-# HBM bytes per launch at the benchmark shape: FETCH_SIZE + WRITE_SIZE from rocprofv3 --pmc, scaled by a 256 MiB
-# copy (profiles/bench_all_fused_subgraphs.md): the fused FFN streaming kernel alone, and the whole entry point
-# (streaming kernel + partial-sum reduction).  Counters cannot be read inside this run; the two figures are
-# re-measured whenever the kernels change.
-FFN_TRAFFIC_BYTES = 85078851
-FFN_TRAFFIC_BYTES_PER_CALL = 138463115
+# HBM bytes per call at the benchmark shape: FETCH_SIZE + WRITE_SIZE from rocprofv3 --pmc, scaled by a 256 MiB copy
+# (profiles/bench_all_fused_subgraphs.md), both products of the FFN chain.  Counters cannot be read inside this run; the
+# figure is re-measured whenever the kernels change.
+FFN_TRAFFIC_BYTES_PER_CALL = 81862913
 
 
 def parse():
@@ -271,25 +269,25 @@ def main():
     roofline = None
     ffn = [c for c in cases if type(c).__name__ == "FfnCase"]
     if ffn and ago.OP_FUSED_FFN in kernel_ms:
-        # The library records events before the streaming kernel, between it and the partial-sum reduction, and
-        # after the reduction.  An event pair reads the bracketed work plus the fixed cost of the pair itself.
+        # The library records events before the chain's first kernel and after its last (and between the two where the
+        # first does all of the chain's products).  A pair reads the bracketed work plus the fixed cost of the pair itself.
         call_s = (kernel_ms[ago.OP_FUSED_FFN] - ev_overhead_ms) * 1e-3
         dur_s = ((ffn_first_ms if ffn_first_ms else kernel_ms[ago.OP_FUSED_FFN]) - ev_overhead_ms) * 1e-3
         ach = ffn[0].flops() / dur_s / 1e12
         ach_call = ffn[0].flops() / call_s / 1e12
-        roofline = {"bound": "mfma", "kernel": "fused_ffn_stream_kernel", "achieved": round(ach, 2),
+        roofline = {"bound": "mfma", "kernel": "gemm_dma_kernel + gemm_split_kernel (ago_fused_ffn)", "achieved": round(ach, 2),
                     "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(ach / PEAK_BF16_TFLOPS, 4),
                     "measured_peak": measured["mfma_bf16_tflops"],
                     "frac_measured": round(ach / measured["mfma_bf16_tflops"], 4),
                     "avg_kernel_us": round(dur_s * 1e6, 2),
-                    "per_call": {"what": "the whole ago_fused_ffn call: streaming kernel + partial-sum reduction kernel",
+                    "per_call": {"what": "the whole ago_fused_ffn call: both products",
                                  "avg_us": round(call_s * 1e6, 2), "achieved": round(ach_call, 2),
                                  "frac": round(ach_call / PEAK_BF16_TFLOPS, 4),
                                  "frac_measured": round(ach_call / measured["mfma_bf16_tflops"], 4),
                                  "traffic": FFN_TRAFFIC_BYTES_PER_CALL},
                     "event_overhead_us": round(ev_overhead_ms * 1e3, 2),
                     "event_sampling": "every %dth step of the timed region" % EVENT_EVERY,
-                    "traffic": FFN_TRAFFIC_BYTES}
+                    "traffic": FFN_TRAFFIC_BYTES_PER_CALL}
         if one_stream and ago.OP_FUSED_FFN in one_stream["kernel_ms"]:
             # the same kernel with the chip to itself (steps back to back on one stream)
             d1 = (one_stream.get("first_ms", one_stream["kernel_ms"][ago.OP_FUSED_FFN]) - ev_overhead_ms) * 1e-3
