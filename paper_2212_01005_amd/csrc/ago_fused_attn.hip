@@ -62,7 +62,7 @@ __device__ __forceinline__ bf16x8 lds_read_vt(const lds_byte* p) {
 // the D = 64 one plus a plane offset.
 template <int NQT, int NSTG, int BIAS /* 0 none, 1 rows that start on a dword, 2 rows that may not */, int NP = 1>
 __global__ __launch_bounds__((2 * NQT + 2) * 64)
-__attribute__((amdgpu_waves_per_eu(NP == 2 ? 2 : (BIAS ? 4 : 3), 4))) void fused_attn_kernel(
+__attribute__((amdgpu_waves_per_eu(NP == 2 ? (NQT > 3 ? 3 : 2) : (BIAS ? 4 : 3), 4))) void fused_attn_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, int S, int heads, int qblocks, int Hh, long stride_b, long stride_h, long stride_s,
     float c /* scale * log2(e); with a bias: scale */, const bf16_t* __restrict__ Bias, long bias_sb, long bias_sh) {
@@ -370,22 +370,24 @@ static hipError_t launch_attn(const void* q, const void* k, const void* v, void*
 }
 
 // Tile configurations: query rows per workgroup (two workgroups share a compute unit except for 3).
-//   0: 96   1: 128   2: 64   3: 192, one workgroup per compute unit, three LDS buffers
+//   0: 96   1: 128   2: 64   3: 192, one workgroup per compute unit, three LDS buffers (head dimension 128: 160, two)
 int fused_attn_num_cfgs() { return 4; }
 
 hipError_t fused_attn(const void* q, const void* k, const void* v, void* o, int B, int Hh, int S,
                       float scale, int tile_cfg, hipStream_t s, long stride_b, long stride_h, long stride_s, int D) {
     if (stride_s == 0) { stride_b = (long)Hh * S * D; stride_h = (long)S * D; stride_s = D; }   // [B][Hh][S][D]
-    if (D == 128) {
-        // two planes: 96 queries per workgroup (eight waves, two per SIMD: 32 query-fragment, 64 output and
-        // 32 score registers per lane need that budget), 64 for configuration 2
-        if (tile_cfg == 2) return launch_attn<2, 2, 0, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s);
-        return launch_attn<3, 2, 0, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s);
-    }
-    if (D != 64) return hipErrorInvalidValue;
+    if (D != 64 && D != 128) return hipErrorInvalidValue;
     if (tile_cfg < 0) {        // built-in choice: the candidate the time model predicts fastest
         AttnPlan plan;
-        tile_cfg = plan_attn(B, Hh, S, 64, -1, &plan) ? plan.cfg : 0;
+        tile_cfg = plan_attn(B, Hh, S, D, -1, &plan) ? plan.cfg : 0;
+    }
+    if (D == 128) {            // two planes, two buffers, one workgroup per compute unit: 160 registers a lane leave three waves to a SIMD
+        switch (tile_cfg) {
+            case 1: return launch_attn<4, 2, 0, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s);
+            case 2: return launch_attn<2, 2, 0, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s);
+            case 3: return launch_attn<5, 2, 0, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s);
+            default: return launch_attn<3, 2, 0, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s);
+        }
     }
     switch (tile_cfg) {
         case 1: return launch_attn<4, 2, 0>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s);
@@ -403,6 +405,8 @@ hipError_t fused_attn_bias(const void* q, const void* k, const void* v, const vo
     // every row starts on a dword: 16-byte loads as they are
     const bool dwords = S % 2 == 0 && bias_sb % 2 == 0 && bias_sh % 2 == 0 && reinterpret_cast<uintptr_t>(bias) % 4 == 0;
     if (D == 128) {
+        // 96 queries: the bias values' registers leave two waves to a SIMD (at three they spill: 128 queries 51 - 60 us
+        // against 57 - 60 on 2 x 32 x 1024, 27.6 against 22.4 on 8 x 12 x 384)
         if (dwords) return launch_attn<3, 2, 1, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs);
         return launch_attn<3, 2, 2, 2>(q, k, v, o, B, Hh, S, stride_b, stride_h, stride_s, scale, s, bs);
     }

@@ -86,6 +86,12 @@ bool plan_conv_chain(int N, int H, int W, int C, int tile_cfg, ChainPlan* out) {
 // ---------------------------------------------------------------------------------------------------
 namespace {
 const int kAttnNqt[4] = {3, 4, 2, 6}, kAttnStages[4] = {2, 2, 2, 3}, kAttnResident[4] = {2, 1, 2, 1};
+// Head dimension 128: 96, 128, 64 or 160 queries, one workgroup per compute unit (LDS), two buffers of two planes.  More
+// queries per workgroup amortise K and V and give the SIMDs three waves to overlap; fewer make more workgroups.  Fill
+// and time per key block, fitted to 12 shapes x 4 candidates (S = 100 ... 4096): mean error 5 %, the choice the best
+// candidate of every shape (2 x 32 x 2000: 183 / 148 / 191 / 165 us; 96 queries alone before).
+const int kAttn128Nqt[4] = {3, 4, 2, 5};
+const double kAttn128FillUs[4] = {5.4, 5.7, 4.2, 6.2}, kAttn128BlockUs[4] = {1.58, 1.90, 1.225, 2.14};
 constexpr double kAttnFillUs = 2.5, kAttnBlockUs = 1.0, kAttnBlockUsPerTile = 0.15;
 }  // namespace
 
@@ -95,10 +101,8 @@ bool plan_attn(int B, int Hh, int S, int D, int tile_cfg, AttnPlan* out) {
     bool have = false;
     for (int cfg = 0; cfg < 4; ++cfg) {
         if (tile_cfg >= 0 && cfg != tile_cfg) continue;
-        // head dimension 128 has the 96- and 64-query workgroups only (two LDS buffers of two planes)
-        if (D == 128 && tile_cfg < 0 && cfg != 0) continue;
         AttnPlan p{};
-        const int nqt = (D == 128 && cfg != 2) ? 3 : kAttnNqt[cfg];
+        const int nqt = D == 128 ? kAttn128Nqt[cfg] : kAttnNqt[cfg];
         p.cfg = cfg; p.queries = 32 * nqt; p.key_block = 128;
         p.stages = D == 128 ? 2 : kAttnStages[cfg];
         p.resident = D == 128 ? 1 : kAttnResident[cfg];
@@ -113,12 +117,13 @@ bool plan_attn(int B, int Hh, int S, int D, int tile_cfg, AttnPlan* out) {
         const double qblocks = (double)ceil_div(S, p.queries);
         p.executed_upstream_macs = upstream_work((double)heads * qblocks * nblk, 1.0, (S / qblocks) * ((double)S / nblk) * D);
         p.algorithmic_upstream_macs = (double)heads * S * S * D;
-        const double per_plane = D / 64.0;
         const long full = wgs / slots, rem = wgs % slots;
-        double t = full * (kAttnFillUs + nblk * per_plane * (kAttnBlockUs + kAttnBlockUsPerTile * nqt * p.resident));
-        if (rem) {      // last, partial round: the compute units hold fewer workgroups
+        double t = full * (kAttnFillUs + nblk * (kAttnBlockUs + kAttnBlockUsPerTile * nqt * p.resident));
+        if (D == 128) {
+            t = p.rounds * (kAttn128FillUs[cfg] + nblk * kAttn128BlockUs[cfg]);
+        } else if (rem) {      // last, partial round: the compute units hold fewer workgroups
             const long r_last = p.resident > 1 ? (ceil_div(rem, kCUs) < p.resident ? ceil_div(rem, kCUs) : p.resident) : 1;
-            t += kAttnFillUs + nblk * per_plane * (kAttnBlockUs + kAttnBlockUsPerTile * nqt * r_last);
+            t += kAttnFillUs + nblk * (kAttnBlockUs + kAttnBlockUsPerTile * nqt * r_last);
         }
         p.predicted_us = kLaunchUs + t;
         if (!have || p.predicted_us < best.predicted_us) { best = p; have = true; }
